@@ -502,3 +502,35 @@ def test_gradients_of_padded_and_ragged_networks(channels, dims):
             assert rel(got[p], want[p]) < 1e-3, p
     assert abs(loss - 0.5 * (la + lb)) < 1e-5 * loss
     W.wl_ptc_destroy(net)
+
+
+@pytest.mark.parametrize("channels,adjoint", [(8, False), (8, True), (5, False), (4, True)])
+def test_network_errors_are_roundings_only(channels, adjoint):
+    """The matrix-core network's error holds no error of the map itself.  d = output - oracle, projected on every
+    path's transported input t_q: E_q = sum_x d t_q^+ / (sum |t_q|^2 / 4).  Roundings that differ from site to site
+    leave |E_q[s, t]|^2 ~ (|d| / |t_q|)^2 / (3 V) per entry, so sqrt(sum over 9 x 16 entries) is about
+    12 (|d| / |t|) / sqrt(3 V), to a few per cent (288 independent numbers); twice that is allowed.  (Products
+    cut off next to a weight of order one gave three to six times it.)"""
+    dims = (12, 10, 14, 22)
+    ph = random_phases(660 + channels)
+    u, lat = lattice(dims, 661, ph)
+    w1, w2 = synth.ptc_weights(channels, seed=662)
+    net = W.wl_ptc_create(w1, w2)
+    w1b, w2b = bf16_round(w1), bf16_round(w2)
+    f = f32(synth.gaussian_spinor(dims, seed=663))
+    out = lat.new(W.WL_FULL, W.WL_F32)
+    W.wl_ptc_apply(lat.ctx, net, out, lat.pack(f, W.WL_FULL, W.WL_F32), adjoint=adjoint)
+    if adjoint:
+        want = ptc.layer_adjoint(ptc.layer_adjoint([f], w2b, u, ph), w1b, u, ph)[0]
+    else:
+        want, _ = ptc.net_apply(f, w1b, w2b, u, ph)
+    d = lat.unpack(out, W.WL_FULL, W.WL_F32).reshape(want.shape) - want
+    n2, total = float(np.linalg.norm(f.ravel())) ** 2, 0.0
+    for p in range(ptc.NPATH):
+        t = ptc.transport(f, u, ph, p)
+        e = np.tensordot(d, t.conj(), axes=([0, 1, 2, 3, 5], [0, 1, 2, 3, 5])) / (n2 / 4)
+        total += float(np.linalg.norm(e)) ** 2
+    noise = 12 * float(np.linalg.norm(d.ravel())) / np.sqrt(n2) / np.sqrt(3 * np.prod(dims))
+    print("map error %.2e, of roundings alone %.2e" % (np.sqrt(total), noise))
+    assert np.sqrt(total) <= 2 * noise
+    W.wl_ptc_destroy(net)
