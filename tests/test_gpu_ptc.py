@@ -534,3 +534,30 @@ def test_network_errors_are_roundings_only(channels, adjoint):
     print("map error %.2e, of roundings alone %.2e" % (np.sqrt(total), noise))
     assert np.sqrt(total) <= 2 * noise
     W.wl_ptc_destroy(net)
+
+
+@pytest.mark.parametrize("channels,adjoint", [(8, False), (4, True), (6, False)])
+def test_network_of_numbers_near_the_largest(channels, adjoint):
+    """Inputs up to the largest FP32 number (above 3.3961e38 a BF16 rounding is infinite), with weights small
+    enough for finite outputs: the network and its adjoint against the oracle, at the FP32 tolerance."""
+    dims = (4, 4, 6, 4)
+    ph = random_phases(670 + channels)
+    u, lat = lattice(dims, 671, ph)
+    w1, w2 = synth.ptc_weights(channels, seed=672)
+    w1, w2 = 0.25 * w1, 0.5 * w2
+    net = W.wl_ptc_create(w1, w2)
+    w1b, w2b = bf16_round(w1), bf16_round(w2)
+    f = np.zeros(dims[::-1] + (4, 3), dtype=np.complex128)
+    big = [float(x) for x in (np.float32(3.4028235e38), np.float32(3.4e38), np.float32(3.3962e38))]
+    f[0, 0, 0, 0, 0, 0], f[1, 3, 2, 1, 3, 2], f[3, 1, 0, 2, 1, 1] = big[0], 1j * big[1], -big[2]
+    out = lat.new(W.WL_FULL, W.WL_F32)
+    W.wl_ptc_apply(lat.ctx, net, out, lat.pack(f, W.WL_FULL, W.WL_F32), adjoint=adjoint)
+    if adjoint:
+        want = ptc.layer_adjoint(ptc.layer_adjoint([f], w2b, u, ph), w1b, u, ph)[0]
+    else:
+        want, _ = ptc.net_apply(f, w1b, w2b, u, ph)
+    got = lat.unpack(out, W.WL_FULL, W.WL_F32).reshape(want.shape)
+    assert np.abs(want).max() < 3e38
+    assert np.isfinite(got).all()
+    assert rel(got / big[0], want / big[0]) < TOL32
+    W.wl_ptc_destroy(net)
