@@ -561,3 +561,45 @@ def test_network_of_numbers_near_the_largest(channels, adjoint):
     assert np.isfinite(got).all()
     assert rel(got / big[0], want / big[0]) < TOL32
     W.wl_ptc_destroy(net)
+
+
+@pytest.mark.parametrize("channels,nrhs,adjoint", [(6, 1, False), (3, 2, True), (2, 1, False), (7, 1, True),
+                                                   (5, 3, False)])
+def test_network_of_tiny_numbers(channels, nrhs, adjoint):
+    """Inputs down to the smallest FP32 numbers: the network of 2^-k f is 2^-k times that of f, at the FP32
+    tolerance (2^-122: BF16 parts alone hold 11 bits of such a number; 2^-136: FP32 holds 13 itself, so the
+    oracle is fed the FP32 numbers and the outputs may be a rounding of 2^-150 per addition off).  One
+    right-hand side of zeros among tiny ones stays zero."""
+    dims = (6, 4, 2, 6)
+    ph = random_phases(680 + channels)
+    u, lat = lattice(dims, 681, ph)
+    w1, w2 = synth.ptc_weights(channels, seed=682)
+    w1 = w1 + random_weights(channels, 1, 683, 0.05)
+    w2 = w2 + random_weights(1, channels, 684, 0.05)
+    net = W.wl_ptc_create(w1, w2)
+    w1b, w2b = bf16_round(w1), bf16_round(w2)
+
+    def apply(fields):
+        out = lat.new(W.WL_FULL, W.WL_F32, nrhs)
+        stack = np.stack([f.reshape(-1, 4, 3) for f in fields])
+        W.wl_ptc_apply(lat.ctx, net, out, lat.pack(stack, W.WL_FULL, W.WL_F32, nrhs), nrhs=nrhs, adjoint=adjoint)
+        got = lat.unpack(out, W.WL_FULL, W.WL_F32, nrhs)
+        return [(got[r] if nrhs > 1 else got).reshape(fields[0].shape) for r in range(nrhs)]
+
+    def oracle(f):
+        if adjoint:
+            return ptc.layer_adjoint(ptc.layer_adjoint([f], w2b, u, ph), w1b, u, ph)[0]
+        return ptc.net_apply(f, w1b, w2b, u, ph)[0]
+
+    base = [f32(synth.gaussian_spinor(dims, seed=685 + r)) for r in range(nrhs)]
+    base[-1] = base[-1] * (nrhs == 1)
+    for k, tol in ((100, TOL32), (112, TOL32), (122, TOL32), (136, 100 * 2.0 ** -14)):
+        fields = [f32(f * 2.0 ** -k) for f in base]
+        for f, got in zip(fields, apply(fields)):
+            want = oracle(f)
+            if np.any(f):
+                print(k, rel(got * 2.0 ** k, want * 2.0 ** k))
+                assert rel(got * 2.0 ** k, want * 2.0 ** k) < tol, k
+            else:
+                assert not np.any(got)
+    W.wl_ptc_destroy(net)
