@@ -603,3 +603,56 @@ def test_network_of_tiny_numbers(channels, nrhs, adjoint):
             else:
                 assert not np.any(got)
     W.wl_ptc_destroy(net)
+
+
+@pytest.mark.parametrize("channels,nrhs,adjoint", [(1, 2, False), (1, 3, True), (9, 2, True), (9, 3, False)])
+def test_networks_on_the_layer_kernels(channels, nrhs, adjoint):
+    """Networks of one or more than eight channels take the layer kernels: M (M^+) of several right-hand sides
+    against the oracle's two layers.  8x6x10x12 x nrhs leaves the gather's last blocks partly empty and their
+    number no multiple of the eight XCDs."""
+    dims = (8, 6, 10, 12)
+    ph = random_phases(690 + channels)
+    u, lat = lattice(dims, 691, ph)
+    w1, w2 = synth.ptc_weights(channels, seed=692)
+    w1 = w1 + random_weights(channels, 1, 693, 0.05)
+    w2 = w2 + random_weights(1, channels, 694, 0.05)
+    w1b, w2b = bf16_round(w1), bf16_round(w2)
+    net = W.wl_ptc_create(w1, w2)
+    fields = [f32(synth.gaussian_spinor(dims, seed=695 + r)) for r in range(nrhs)]
+    stack = np.stack([f.reshape(-1, 4, 3) for f in fields])
+    out = lat.new(W.WL_FULL, W.WL_F32, nrhs)
+    W.wl_ptc_apply(lat.ctx, net, out, lat.pack(stack, W.WL_FULL, W.WL_F32, nrhs), nrhs=nrhs, adjoint=adjoint)
+    got = lat.unpack(out, W.WL_FULL, W.WL_F32, nrhs)
+    for r, f in enumerate(fields):
+        if adjoint:
+            want = ptc.layer_adjoint(ptc.layer_adjoint([f], w2b, u, ph), w1b, u, ph)[0]
+        else:
+            want, _ = ptc.net_apply(f, w1b, w2b, u, ph)
+        assert rel(got[r].reshape(want.shape), want) < TOL32, r
+    W.wl_ptc_destroy(net)
+
+
+@pytest.mark.parametrize("channels,dims", [(8, (10, 14, 6, 22)), (3, (10, 14, 6, 22)), (2, (18, 14, 22, 24))])
+def test_gradients_where_blocks_take_several_tiles(channels, dims):
+    """The fused gradient kernel with more than 512 tiles of 16 points, where a block takes several: 10x14x6x22
+    has 1,156 tiles, three a block (the last block one, one block across the parities, a partial tile at the end
+    of each parity), 18x14x22x24 has 8,316, sixteen a block (the last block twelve).  A tile left out would be
+    1e-4 to 1e-3 of the sum; FP32 arithmetic with the oracle's BF16 weights: TOL32 normwise."""
+    ph = random_phases(700 + channels)
+    u, lat = lattice(dims, 701, ph)
+    w1, w2 = synth.ptc_weights(channels, seed=702)
+    w1 = w1 + random_weights(channels, 1, 703, 0.05)
+    w2 = w2 + random_weights(1, channels, 704, 0.05)
+    net = W.wl_ptc_create(w1, w2)
+    r, e = (f32(synth.gaussian_spinor(dims, seed=705 + k)) for k in range(2))
+    W.wl_ptc_accumulate(lat.ctx, net, lat.pack(r, W.WL_FULL, W.WL_F32), lat.pack(e, W.WL_FULL, W.WL_F32), 1.0)
+    g1, g2 = W.wl_ptc_get_grads(net, channels)
+    loss = W.wl_ptc_step(net, 1e-3)
+    want_loss, a1, a2 = ptc.loss_and_grads([(r, e)], bf16_round(w1), bf16_round(w2), u, ph)
+    print("gradient errors", rel(g1, a1), rel(g2, a2), "loss", abs(loss - want_loss) / want_loss)
+    for got, want in ((g1, a1), (g2, a2)):
+        assert rel(got, want) < TOL32
+        for p in range(9):
+            assert rel(got[p], want[p]) < 1e-4, p
+    assert abs(loss - want_loss) < 1e-5 * want_loss
+    W.wl_ptc_destroy(net)
