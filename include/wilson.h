@@ -115,7 +115,11 @@ wl_status wl_ctx_prepare_links(wl_ctx *ctx, wl_prec prec, int recon);
  *           forward and backward hops run in the two halves of a wavefront,
  *           each half storing two spin components; with 16-bit storage the
  *           halves first agree on the point's norm, so the stored bytes are
- *           those of the one-thread store)
+ *           those of the one-thread store).  FP64 launches of up to 8,192 and
+ *           FP32 launches of up to 16,384 output points x right-hand sides run
+ *           eight threads per point with tps = 2 (one hop each, the same bits;
+ *           measured 8-20 % faster there), unless another block than the
+ *           default, nt = 1 or an occ cap is asked for: such a launch has two
  *   tchunk  processing order of the output sites: 0 = even/odd index order
  *           (t slowest); k > 0 = the lattice is cut into chunks of k time
  *           slices and each chunk is walked with z slowest, so that the

@@ -134,7 +134,7 @@ wl_status wli::cg_iteration(CGRun &R, bool reliable) {
     const int tps = effective_tps(R.prec, cfg);
     const bool fused = !reliable && effective_rpt(cfg, R.nrhs, tps) == 1;
     // both scalar steps inside the launches that use them, on lattices small enough
-    const bool fold = fused && cg_fold_ok(R.prec, tps, R.c->Vh * (long)R.nrhs, R.nh, R.nrhs);
+    const bool fold = fused && cg_fold_ok(R.prec, tps, cfg, R.c->Vh * (long)R.nrhs, R.nh, R.nrhs);
     if (!fold) HIP_TRY(cg_alpha(R.sc, R.nrhs, R.partials, R.stride, nblk, R.done, R.s));
     if (fused) {
         // the last operator stage updates r in place (r -= alpha A p, ||r||^2) instead of
@@ -173,7 +173,7 @@ std::vector<uintptr_t> wli::graph_key(const CGRun &R) {
             (uintptr_t)R.tmp,
             (uintptr_t)R.partials, (uintptr_t)R.stride, (uintptr_t)R.sc, (uintptr_t)R.done,
             (uintptr_t)R.nblk_blas, (uintptr_t)g.block, (uintptr_t)g.swizzle, (uintptr_t)g.tps,
-            (uintptr_t)g.tchunk, (uintptr_t)(g.nt + 1), (uintptr_t)g.rpt};
+            (uintptr_t)g.tchunk, (uintptr_t)(g.nt + 1), (uintptr_t)g.rpt, (uintptr_t)g.occ, (uintptr_t)g.sweep};
 }
 
 // Capture one plain CG iteration on R.s (the context's own stream) into a

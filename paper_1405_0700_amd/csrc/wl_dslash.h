@@ -84,6 +84,10 @@ struct LaunchCfg {
                        // launches within L2)
 };
 
+// default block of the two-threads-per-point launch: FP64 128 threads, FP32 256 (2 % faster
+// than 128 at 1, 4 and 12 rhs)
+constexpr int hop_default_block(int prec) { return prec == WL_F64 ? 128 : 256; }
+
 // dynamic LDS bytes per block that cap a launch of `block` threads at `occ`
 // waves per SIMD (160 KB of LDS per CU, 4 SIMDs); 0 for no cap
 unsigned occupancy_lds(int occ, int block, unsigned static_lds);
@@ -139,11 +143,14 @@ hipError_t launch_hop_batch(int prec, int recon, bool dagger, int epi, bool nt, 
 // Eight threads per point (one hop each) in place of two, FP64 and FP32 storage: when
 // the launch's points are too few to fill the chip (bit-identical results).  Up to 8,192
 // FP64 points (4.8 against 5.2 us; 9,280 points 5.7 against 5.3 us) and 16,384 FP32 points
-// (13,824: 4.3 against 4.8 us; from 18,560 on level, at 65,536 11 against 9.9 us).
+// (13,824: 4.3 against 4.8 us; from 18,560 on level, at 65,536 11 against 9.9 us).  It has
+// a block of its own, no occupancy cap and no non-temporal hints: a launch configuration that
+// asks for another block, a cap or the hints gets the two-threads-per-point kernel.
 constexpr int HOP_WIDE_BLOCK = 256;
-inline bool hop_wide(int prec, int tps, long npts, int nparity) {
+inline bool hop_wide(int prec, int tps, const LaunchCfg &cfg, long npts, int nparity) {
     const long most = prec == WL_F64 ? 8192 : 16384;
-    return tps == 2 && (prec == WL_F64 || prec == WL_F32) && npts * nparity <= most;
+    return tps == 2 && (prec == WL_F64 || prec == WL_F32) && cfg.block == hop_default_block(prec) && cfg.occ == 0 &&
+           cfg.nt != 1 && npts * nparity <= most;
 }
 // CG's alpha step folded into the launch that uses alpha (EPI_CGR): every block adds the
 // partial sums of ||q||^2 itself and forms alpha = rho / ||q||^2, block 0 stores it; part ==
@@ -155,9 +162,10 @@ struct HopFold {
 };
 // A launch of its own costs a scalar step 2.3 us and a launch; 256 partial sums added by
 // every block cost the launch 0.3 us.  8^3x16 FP64: an iteration of three launches in
-// place of five, 20 against 27 us with the finer x / p update.
-inline bool cg_fold_ok(int prec, int tps, long npts, int nparity, int nrhs) {
-    return hop_wide(prec, tps, npts, nparity) && (npts * 8 + HOP_WIDE_BLOCK - 1) / HOP_WIDE_BLOCK * nparity * nrhs <= 1024;
+// place of five, 20 against 27 us with the finer x / p update.  The eight-threads-per-point
+// kernel is the one that has the fold, hence its limits.
+inline bool cg_fold_ok(int prec, int tps, const LaunchCfg &cfg, long npts, int nparity, int nrhs) {
+    return hop_wide(prec, tps, cfg, npts, nparity) && (npts * 8 + HOP_WIDE_BLOCK - 1) / HOP_WIDE_BLOCK * nparity * nrhs <= 1024;
 }
 hipError_t launch_hop_wide(int prec, int recon, bool dagger, int epi, const HopArgs &a, int nparity, const HopFold &f,
                            hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
@@ -185,7 +193,7 @@ inline int effective_sweep(const LaunchCfg &cfg, int nrhs, int tps, int lt, int 
 // slices, sites_per_slice sites of one parity per slice)
 inline long hop_launch_blocks(int tps, const LaunchCfg &cfg, long npts, int nrhs, int lt, long sites_per_slice,
                               int prec, int nparity) {
-    if (hop_wide(prec, tps, npts, nparity)) return hop_blocks(npts, HOP_WIDE_BLOCK, 8);
+    if (hop_wide(prec, tps, cfg, npts, nparity)) return hop_blocks(npts, HOP_WIDE_BLOCK, 8);
     const int r = effective_rpt(cfg, nrhs, tps);
     if (const int sw = lt > 0 ? effective_sweep(cfg, nrhs, tps, lt, prec) : 0)
         return hop_blocks(sites_per_slice * nrhs, cfg.block, 1) * ((lt + sw - 1) / sw);

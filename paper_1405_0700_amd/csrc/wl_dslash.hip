@@ -232,7 +232,7 @@ hipError_t launch_hop(int prec, int recon, bool dagger, int epi, HopArgs &a, int
     const int rpt = effective_rpt(cfg, a.nrhs, tps);
     if (rpt > 1 && (a.nrhs > 256 || block < 64 || (epi & EPI_CGR))) return hipErrorInvalidValue;
     a.sweep = effective_sweep(cfg, a.nrhs, tps, a.g.L[3], prec);
-    if (hop_wide(prec, tps, a.npts, nparity))
+    if (hop_wide(prec, tps, cfg, a.npts, nparity))
         return launch_hop_wide(prec, recon, dagger, epi, a, nparity, fold ? *fold : HopFold{}, stream, ev0, ev1);
     if (fold) return hipErrorInvalidValue;
     dim3 grid((unsigned)hop_launch_blocks(tps, cfg, a.npts, a.nrhs, a.g.L[3], a.g.st, prec, nparity),
