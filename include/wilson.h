@@ -141,7 +141,8 @@ wl_status wl_ctx_prepare_links(wl_ctx *ctx, wl_prec prec, int recon);
  *   nt      1: non-temporal hints on the link loads and output stores (they
  *           keep the single-use link stream from evicting re-read spinors from
  *           L2, but also bypass the Infinity Cache); 0: off; -1: on when the
- *           launch's links and spinor fields exceed 300 MB
+ *           launch's links and spinor fields exceed 300 MB (200 MB for the FP64
+ *           refreshes of a solve that iterates in a 16-bit format)
  *   rpt     right-hand sides per thread: 1, 2, 3 or 4.  With rpt > 1 (and
  *           tps = 1) a thread computes rpt consecutive right-hand sides of one
  *           site and applies each link it loads to all of them; a launch whose

@@ -36,7 +36,7 @@ static wl_status fold_x(CGRun &R) {
 wl_status wli::true_residual(CGRun &R) {
     wl_status st = fold_x(R);
     if (st) return st;
-    const double nt_limit = R.prec == WL_F64 ? NT_WORKING_SET : NT_WORKING_SET_REFRESH;
+    const double nt_limit = nt_refresh_limit(R.prec);
     st = apply_m(R.c, R.op, false, R.kappa, WL_F64, 18, R.nrhs, R.thi, R.x, R.tmphi, nullptr, 0, nullptr,
                            R.s, nullptr, R.mu, nt_limit);
     if (st) return st;

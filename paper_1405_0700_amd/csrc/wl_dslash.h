@@ -99,10 +99,12 @@ unsigned occupancy_lds(int occ, int block, unsigned static_lds);
 // 24^3x48 FP64 (573 MB) 216 / 195; between, 354 and 377 MB, level.  e/o solves alike:
 // 16x16x20x40 FP64 with 2 rhs (236 MB) 42.9 / 46.7 ms, 32^3x64 FP16 (365 MB) 127.5 / 120.7.
 constexpr double NT_WORKING_SET = 300e6;
-// The same for the FP64 refreshes of a mixed-precision solve, whose fields come between the
-// iterations' smaller ones: 16x24x28x30, FP16-size storage, 279 MB refreshes 14.02 ms hinted,
-// 14.11 cached.
-constexpr double NT_WORKING_SET_REFRESH = 200e6;
+// The line for the FP64 operator of a solve that iterates in storage `prec`.  16-bit storage:
+// cached, an FP64 refresh evicts the iterations' fields, which are a quarter of its own; solves
+// with hinted refreshes of 210 to 320 MB are 0.5 to 1.5 % faster (7 lattices from 16x20x24x32
+// to 20x24x24x32 x 3 formats, 21 of 21, medians of 7, runs 0.1 % apart; BF16 at 16x24x28x30,
+// 279 MB, 13.78 against 13.93 ms).  FP32 storage, same lattices: 0.9956 to 1.0035, level.
+constexpr double nt_refresh_limit(int prec) { return prec >= WL_F16N ? 200e6 : NT_WORKING_SET; }
 // whether a launch uses the non-temporal hints
 bool use_nontemporal(int prec, const LaunchCfg &cfg, const HopArgs &a, int nparity, int epi,
                      double limit = NT_WORKING_SET);

@@ -2,7 +2,8 @@
 //  * the eight-threads-per-point kernel takes small FP64 / FP32 launches of the default
 //    configuration, and CG's scalar steps fold into them;
 //  * a configuration that asks for another block, an occupancy cap or non-temporal hints gets
-//    the two-threads-per-point kernel with that block.
+//    the two-threads-per-point kernel with that block;
+//  * FP64 refreshes are hinted from 200 MB on between 16-bit iterations, else like any launch.
 // Prints "ok" and exits 0, or prints the first failure and exits 1.
 #include <cstdio>
 
@@ -45,11 +46,13 @@ int main() {
         }
         CHECK(hop_launch_blocks(2, def, most + 1, 1, 8, most / 8, prec, 1) == (2 * (most + 1) + def.block - 1) / def.block);
         CHECK(!cg_fold_ok(prec, 2, def, most + 1, 1, 1));
+        CHECK(nt_refresh_limit(prec) == NT_WORKING_SET);
     }
     for (int prec : {(int)WL_F16N, (int)WL_BF16N, (int)WL_I16N}) {
         LaunchCfg c;
         c.tps = 2;
         CHECK(hop_launch_blocks(2, c, 1024, 1, 8, 128, prec, 1) == 8);
+        CHECK(nt_refresh_limit(prec) == 200e6);
     }
     printf("ok\n");
     return 0;
