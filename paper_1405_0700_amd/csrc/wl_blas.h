@@ -23,6 +23,65 @@ struct CGScalars {
     int iter_prev;   // block of the update that replaces them
 };
 
+// The scalar rules of an iteration, shared by the kernels that run them by themselves and the
+// hopping and vector launches they are folded into.
+// alpha = rho / <p, A p>, with ok = 0 (and alpha = 0) for a breakdown
+struct CGAlpha {
+    double alpha;
+    bool ok;
+};
+__device__ __forceinline__ CGAlpha cg_alpha_rule(double rho, double pap) {
+    const bool ok = pap > 0.0 && isfinite(pap) && isfinite(rho);
+    return {ok ? rho / pap : 0.0, ok};
+}
+// keep it, for a system that is iterating; after a breakdown it leaves the active count at the
+// beta step of this iteration
+__device__ __forceinline__ void cg_alpha_keep(CGScalars &c, double pap, const CGAlpha &a) {
+    c.pap = pap;
+    c.alpha = a.alpha;
+    if (!a.ok) {
+        c.status = WL_BREAKDOWN;
+        c.active = 0;
+        c.leaving = 1;
+    }
+}
+// beta = s / rho for s = ||r||^2 after iteration `iter` (restart: 0), and whether the system goes
+// on; status counts only if it does not
+struct CGBeta {
+    double beta;
+    int status;
+    bool go;
+};
+__device__ __forceinline__ CGBeta cg_beta_rule(double s, double rho, bool restart, double target, int iter, int maxiter) {
+    if (!isfinite(s)) return {0.0, WL_BREAKDOWN, false};
+    const double beta = restart ? 0.0 : s / rho;
+    if (s <= target) return {beta, WL_OK, false};
+    return {beta, WL_NOT_CONVERGED, iter < maxiter};
+}
+// keep it (mode 0: a plain step, else a refresh, which restarts the rho_max record); a system that
+// stops leaves the active count
+__device__ __forceinline__ void cg_beta_keep(CGScalars &c, double s, const CGBeta &b, int iter, int mode, int *count) {
+    c.beta = b.beta;
+    c.iter = iter;
+    if (isfinite(s)) {
+        c.rho = s;
+        c.rho_max = mode ? s : fmax(c.rho_max, s);
+    }
+    if (!b.go) {
+        c.status = b.status;
+        c.active = 0;
+        atomicSub(count, 1);
+    }
+}
+// a system that is not iterating: beta = 0, and a breakdown of this iteration leaves the count
+__device__ __forceinline__ void cg_beta_idle(CGScalars &c, int *count) {
+    c.beta = 0.0;
+    if (c.leaving) {
+        c.leaving = 0;
+        atomicSub(count, 1);
+    }
+}
+
 struct VecArgs {
     void *v[4][2];     // up to 4 fields, each given per half (half 0 / half 1)
     long n;            // points per half

@@ -230,42 +230,19 @@ __global__ void __launch_bounds__(256) k_cg_xp_unit(const CGVecArgs A) {
         r = ((const V *)a.r[h])[u];
     }
     if constexpr (FOLD) {
-        // the beta step of cg_beta (mode 0).  Read here: alpha, rho_prev, iter_prev, target,
-        // maxiter, none of which changes in this launch; block 0 writes the rest.
+        // the beta step (mode 0).  Every block reads alpha, rho_prev, iter_prev, target and
+        // maxiter, none of which changes in this launch; block 0 reads and writes the rest.
         for (int k = threadIdx.x >> 6; k < a.nrhs; k += 4) {
             const double s = wave_partials(a.partials + k * a.stride, a.nblk);
             if ((threadIdx.x & 63) == 0) {
                 CGScalars &c = a.sc[k];
-                const double alpha = c.alpha;
-                double beta = 0.0;
-                int go = 0, status = WL_NOT_CONVERGED;
-                if (alpha != 0.0) {
-                    const bool fin = isfinite(s);
-                    const bool met = fin && s <= c.target, out = c.iter_prev + 1 >= c.maxiter;
-                    status = !fin ? WL_BREAKDOWN : (met ? WL_OK : WL_NOT_CONVERGED);
-                    go = fin && !met && !out;
-                    if (fin) beta = s / c.rho_prev;
-                }
-                s_alpha[k] = alpha;
-                s_beta[k] = beta;
-                if (!go && alpha != 0.0) s_beta[k] = __builtin_nan("");  // stopped: p stays
+                const int iter = c.iter_prev + 1;
+                const CGBeta b = cg_beta_rule(s, c.rho_prev, false, c.target, iter, c.maxiter);
+                s_alpha[k] = c.alpha;
+                s_beta[k] = b.go ? b.beta : __builtin_nan("");  // stopped: p stays
                 if (lb == 0) {
-                    c.beta = beta;
-                    if (alpha != 0.0) {
-                        c.iter = c.iter_prev + 1;
-                        if (status != WL_BREAKDOWN) {
-                            c.rho = s;
-                            c.rho_max = fmax(c.rho_max, s);
-                        }
-                        c.status = status;
-                        if (!go) {
-                            c.active = 0;
-                            atomicSub(a.count, 1);
-                        }
-                    } else if (c.leaving) {
-                        c.leaving = 0;
-                        atomicSub(a.count, 1);
-                    }
+                    if (c.active) cg_beta_keep(c, s, b, iter, 0, a.count);
+                    else cg_beta_idle(c, a.count);
                 }
             }
         }
@@ -538,60 +515,26 @@ __device__ __forceinline__ void cg_alpha_step(CGScalars &c, const double *partia
         return;
     }
     const double s = sum_partials(partials, nblk, lds);
-    if (threadIdx.x == 0) {
-        c.pap = s;
-        if (!(s > 0.0) || !isfinite(s) || !isfinite(c.rho)) {
-            c.status = WL_BREAKDOWN;
-            c.active = 0;
-            c.alpha = 0.0;
-            // leaves the count at the beta step of this iteration
-            c.leaving = 1;
-        } else {
-            c.alpha = c.rho / s;
-        }
-    }
+    if (threadIdx.x == 0) cg_alpha_keep(c, s, cg_alpha_rule(c.rho, s));
 }
 
 __device__ __forceinline__ void cg_beta_step(CGScalars &c, const double *partials, long nblk, int *count, int mode) {
     if (*count == 0) return;
     __shared__ double lds[16];
     if (!c.active) {
-        if (threadIdx.x == 0) {
-            c.beta = 0.0;
-            if (c.leaving) {
-                c.leaving = 0;
-                atomicSub(count, 1);
-            }
-        }
+        if (threadIdx.x == 0) cg_beta_idle(c, count);
         return;
     }
     const double s = sum_partials(partials, nblk, lds);
     if (threadIdx.x == 0) {
-        c.beta = 0.0;
-        c.iter += 1;
-        if (!isfinite(s)) {
-            c.status = WL_BREAKDOWN;
-            c.active = 0;
-        } else {
-            // mode 0: plain step; 1: the residual was just refreshed in FP64 (restart
-            // the rho_max record); 2: also restart the search direction.  In mode 1 a
-            // refresh that finds the true residual more than twice the iterated one
-            // (the iterated residual had drifted far below it) restarts the direction
-            // as well: the old direction then says nothing about the new residual, and
-            // beta = rho'/rho would be large and let it dominate.
-            const bool restart = mode == 2 || (mode == 1 && s > 4.0 * c.rho_iter);
-            c.beta = restart ? 0.0 : s / c.rho;
-            c.rho = s;
-            c.rho_max = mode ? s : fmax(c.rho_max, s);
-            if (s <= c.target) {
-                c.status = WL_OK;
-                c.active = 0;
-            } else if (c.iter >= c.maxiter) {
-                c.status = WL_NOT_CONVERGED;
-                c.active = 0;
-            }
-        }
-        if (!c.active) atomicSub(count, 1);
+        // mode 0: plain step; 1: the residual was just refreshed in FP64 (restart
+        // the rho_max record); 2: also restart the search direction.  In mode 1 a
+        // refresh that finds the true residual more than twice the iterated one
+        // (the iterated residual had drifted far below it) restarts the direction
+        // as well: the old direction then says nothing about the new residual, and
+        // beta = rho'/rho would be large and let it dominate.
+        const bool restart = mode == 2 || (mode == 1 && s > 4.0 * c.rho_iter);
+        cg_beta_keep(c, s, cg_beta_rule(s, c.rho, restart, c.target, c.iter + 1, c.maxiter), c.iter + 1, mode, count);
     }
 }
 

@@ -994,7 +994,7 @@ __global__ void __launch_bounds__(HOP_WIDE_BLOCK) hop_wide_kernel(const HopArgs 
     __shared__ double s_alpha[EPI & EPI_CGR ? 64 : 1];
     if constexpr (EPI & EPI_CGR) {
         if (fold.part) {
-            // the alpha step of cg_alpha.  A breakdown found by block 0 clears `active` while other
+            // the alpha step.  A breakdown found by block 0 clears `active` while other
             // blocks read it: they find alpha = 0 either way.
             for (int k = threadIdx.x >> 6; k < a.nrhs; k += HOP_WIDE_BLOCK / 64) {
                 const double *pk = fold.part + k * fold.stride;
@@ -1006,20 +1006,13 @@ __global__ void __launch_bounds__(HOP_WIDE_BLOCK) hop_wide_kernel(const HopArgs 
                     CGScalars &sc = fold.sc[k];
                     const double rho = sc.rho;
                     const bool on = live != 0 && sc.active != 0;
-                    const bool ok = sum > 0.0 && isfinite(sum) && isfinite(rho);
-                    s_alpha[k] = on && ok ? rho / sum : 0.0;
+                    const CGAlpha al = cg_alpha_rule(rho, sum);
+                    s_alpha[k] = on ? al.alpha : 0.0;
                     if (lb == 0 && blockIdx.y == 0) {
-                        sc.alpha = s_alpha[k];
                         sc.rho_prev = rho;
                         sc.iter_prev = sc.iter;
-                        if (on) {
-                            sc.pap = sum;
-                            if (!ok) {
-                                sc.status = WL_BREAKDOWN;
-                                sc.active = 0;
-                                sc.leaving = 1;  // leaves the count at the beta step
-                            }
-                        }
+                        if (on) cg_alpha_keep(sc, sum, al);
+                        else sc.alpha = 0.0;
                     }
                 }
             }
