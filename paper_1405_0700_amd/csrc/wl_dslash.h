@@ -129,7 +129,7 @@ hipError_t launch_hop(int prec, int recon, bool dagger, int epi, HopArgs &a, int
 // output parity); tiles of system k: per_par[k] blocks of `block` points per
 // output parity, np[k] parities; start[k] = first tile of system k in the
 // concatenated list, start[nsys] = ntiles.
-constexpr int BATCH_MAX = 8;
+constexpr int BATCH_MAX = CG_SYS_MAX;  // the scalar and vector launches of a batch take them all at once
 struct BatchArgs {
     HopArgs sys[BATCH_MAX];
     long start[BATCH_MAX + 1];
