@@ -67,7 +67,6 @@ struct PackArgs {
     int ns;      // canonical sites of a block (even)
     long nsite;  // canonical sites of the field
     FastDiv f_run;  // 12 ns: 16-byte units of a block's run of one right-hand side
-    int direct;     // pack: a thread reads its point's 192 bytes itself
 };
 
 // unit e of the block's canonical runs: its right-hand side, site in the run and component
@@ -109,16 +108,6 @@ __global__ void __launch_bounds__(PACK_POINTS) k_pack(const PackArgs a, void *ds
     const int nloc = (int)min((long)a.ns, a.nsite - s0);
     int h, slot;
     long pt;
-    if (a.direct) {
-        if (!pack_point(a, s0, nloc, threadIdx.x, h, pt, slot)) return;
-        const int sl = slot / a.nrhs;
-        const double2 *from = (const double2 *)src + ((long)(slot - sl * a.nrhs) * a.nsite + s0 + sl) * 12;
-        cpx<T> v[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) v[k] = {(T)from[k].x, (T)from[k].y};
-        SpinorIO<SP>::store((char *)dst + h * a.half_bytes, pt, v);
-        return;
-    }
     const int total = a.nrhs * a.f_run.d;
     for (int e0 = threadIdx.x; e0 < total; e0 += PACK_BURST * PACK_POINTS) {
         v2d d[PACK_BURST];
@@ -141,6 +130,31 @@ __global__ void __launch_bounds__(PACK_POINTS) k_pack(const PackArgs a, void *ds
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
         const double2 d = lds[slot * 13 + k];
+        v[k] = {(T)d.x, (T)d.y};
+    }
+    SpinorIO<SP>::store((char *)dst + h * a.half_bytes, pt, v);
+}
+
+// a thread per internal point, which reads its point's 192 bytes itself (see pack_direct)
+constexpr int PACK_DIRECT_BLOCK = 256;
+template <int SP>
+__global__ void __launch_bounds__(PACK_DIRECT_BLOCK) k_pack_direct(const PackArgs a, void *dst, const double *src) {
+    using T = typename SpinorIO<SP>::real;
+    const int h = blockIdx.y;
+    const long pt = (long)blockIdx.x * PACK_DIRECT_BLOCK + threadIdx.x;
+    if (pt >= (long)a.g.vh * a.nrhs) return;
+    const int i = (int)(pt / a.nrhs), rhs = (int)(pt - (long)i * a.nrhs);
+    long site = i;
+    if (a.subset == WL_FULL) {
+        int c[4];
+        eo_coords(a.g, i, h, c);
+        site = c[0] + (long)a.g.L[0] * (c[1] + (long)a.g.L[1] * (c[2] + (long)a.g.L[2] * c[3]));
+    }
+    const double2 *from = (const double2 *)src + (rhs * a.nsite + site) * 12;
+    cpx<T> v[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        const double2 d = from[k];
         v[k] = {(T)d.x, (T)d.y};
     }
     SpinorIO<SP>::store((char *)dst + h * a.half_bytes, pt, v);
@@ -171,6 +185,22 @@ __global__ void __launch_bounds__(PACK_POINTS) k_unpack(const PackArgs a, double
     }
 }
 
+// Whether a thread reads its point's 192 bytes itself (k_pack_direct) instead of going through
+// LDS.  LDS pays where the source's lines would come from HBM more than once (many sites
+// in flight, both parities of a line read by different blocks) and the launch is long enough
+// for two phases a block; a half field's wave reads whole stretches anyway.  Times of direct
+// over LDS, 18 counts of right-hand sides on 7 lattices from 8^4 to 32^4:
+//   full fields, FP64 and FP32: below 72,000 points 0.77 to 1.02 (once 1.13), from there 0.92 to
+//     1.37 (16^3x32, 12 rhs, FP32 103 against 89 us), 33 rhs 0.83 to 1.16; 16-bit formats: below
+//     330,000 points 0.79 to 1.23, 2 and 3 rhs 0.86 to 1.18, the rest 0.96 to 1.45;
+//   half fields: below 700,000 points or 12 rhs (16-bit: 24) 0.72 to 1.12 (0.92 in the middle), the
+//     rest 0.93 to 1.26 (16^3x32, 24 rhs, FP32 105 against 85 us).
+static bool pack_direct(int prec, int subset, int nrhs, long vh) {
+    const bool narrow = prec != WL_F64 && prec != WL_F32;
+    const long points = vh * nrhs * (subset == WL_FULL ? 2 : 1);
+    if (subset != WL_FULL) return points < 700000 || nrhs < (narrow ? 24 : 12);
+    return narrow ? points < 330000 || nrhs == 2 || nrhs == 3 : points < 72000 || (nrhs > 32 && nrhs % 2);
+}
 static PackArgs pack_args(const wl_ctx *c, int subset, size_t hb, int nrhs, dim3 *grid) {
     PackArgs a;
     a.g = c->g;
@@ -180,9 +210,6 @@ static PackArgs pack_args(const wl_ctx *c, int subset, size_t hb, int nrhs, dim3
     a.ns = PACK_POINTS / nrhs & ~1;  // nrhs <= 64
     a.nsite = subset == WL_FULL ? c->V : c->Vh;
     a.f_run = make_fastdiv(12 * a.ns);
-    // a half field of few right-hand sides: a wave's points are a few whole stretches of the
-    // source anyway (24^3x48, 1 rhs FP32 16.1 against 17.2 us, 4 rhs FP16 58.7 against 63.4 us)
-    a.direct = subset != WL_FULL && nrhs <= 4;
     *grid = dim3((unsigned)((a.nsite + a.ns - 1) / a.ns));
     return a;
 }
@@ -204,17 +231,18 @@ __global__ void __launch_bounds__(256) k_link_convert(void *dst, size_t dslab, c
 }
 
 template <template <int> class K, typename... A>
-static hipError_t launch_prec(int prec, dim3 grid, hipStream_t s, A... args) {
+static hipError_t launch_prec(int prec, dim3 grid, int block, hipStream_t s, A... args) {
     switch (prec) {
-    case WL_F64: hipLaunchKernelGGL(K<WL_F64>::fn, grid, dim3(PACK_POINTS), 0, s, args...); break;
-    case WL_F32: hipLaunchKernelGGL(K<WL_F32>::fn, grid, dim3(PACK_POINTS), 0, s, args...); break;
-    case WL_F16N: hipLaunchKernelGGL(K<WL_F16N>::fn, grid, dim3(PACK_POINTS), 0, s, args...); break;
-    case WL_BF16N: hipLaunchKernelGGL(K<WL_BF16N>::fn, grid, dim3(PACK_POINTS), 0, s, args...); break;
-    case WL_I16N: hipLaunchKernelGGL(K<WL_I16N>::fn, grid, dim3(PACK_POINTS), 0, s, args...); break;
+    case WL_F64: hipLaunchKernelGGL(K<WL_F64>::fn, grid, dim3(block), 0, s, args...); break;
+    case WL_F32: hipLaunchKernelGGL(K<WL_F32>::fn, grid, dim3(block), 0, s, args...); break;
+    case WL_F16N: hipLaunchKernelGGL(K<WL_F16N>::fn, grid, dim3(block), 0, s, args...); break;
+    case WL_BF16N: hipLaunchKernelGGL(K<WL_BF16N>::fn, grid, dim3(block), 0, s, args...); break;
+    case WL_I16N: hipLaunchKernelGGL(K<WL_I16N>::fn, grid, dim3(block), 0, s, args...); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
+template <int SP> struct PackDirectK { static constexpr auto fn = k_pack_direct<SP>; };
 template <int SP> struct PackK { static constexpr auto fn = k_pack<SP>; };
 template <int SP> struct UnpackK { static constexpr auto fn = k_unpack<SP>; };
 
@@ -411,7 +439,12 @@ extern "C" wl_status wl_pack_spinor(const wl_ctx *c, void *dst, const double *sr
     if (overlap(dst, hb * nh, src, (size_t)c->Vh * nh * nrhs * 24 * 8)) return fail(WL_ERR_ARG, "dst and src overlap");
     dim3 grid;
     const PackArgs a = pack_args(c, subset, hb, nrhs, &grid);
-    HIP_TRY((launch_prec<PackK>(prec, grid, (hipStream_t)stream, a, dst, src)));
+    if (pack_direct(prec, subset, nrhs, c->Vh)) {
+        grid = dim3((unsigned)((c->Vh * nrhs + PACK_DIRECT_BLOCK - 1) / PACK_DIRECT_BLOCK), nh);
+        HIP_TRY((launch_prec<PackDirectK>(prec, grid, PACK_DIRECT_BLOCK, (hipStream_t)stream, a, dst, src)));
+        return WL_OK;
+    }
+    HIP_TRY((launch_prec<PackK>(prec, grid, PACK_POINTS, (hipStream_t)stream, a, dst, src)));
     return WL_OK;
 }
 
@@ -427,7 +460,7 @@ extern "C" wl_status wl_unpack_spinor(const wl_ctx *c, double *dst, const void *
     if (overlap(dst, (size_t)c->Vh * nh * nrhs * 24 * 8, src, hb * nh)) return fail(WL_ERR_ARG, "dst and src overlap");
     dim3 grid;
     const PackArgs a = pack_args(c, subset, hb, nrhs, &grid);
-    HIP_TRY((launch_prec<UnpackK>(prec, grid, (hipStream_t)stream, a, dst, src)));
+    HIP_TRY((launch_prec<UnpackK>(prec, grid, PACK_POINTS, (hipStream_t)stream, a, dst, src)));
     return WL_OK;
 }
 

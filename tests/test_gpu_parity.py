@@ -841,3 +841,34 @@ def test_default_stream_argument_is_torchs_current_stream():
     with torch.cuda.stream(s):
         assert W._stream(None) == s.cuda_stream != torch.cuda.default_stream().cuda_stream
     assert W._stream(s) == s.cuda_stream and W._stream(7) == 7
+
+
+@pytest.mark.parametrize("dims,nrhs,subset,precs", [
+    ((8, 8, 8, 8), 17, "full", "f64 f32 f16n"),          # 69,632 points: direct
+    ((10, 14, 6, 22), 4, "full", "f64 f32 f16n"),        # 73,920: LDS for FP64 / FP32
+    ((12, 12, 12, 24), 8, "full", "f32 bf16n i16n"),     # 331,776: LDS for the 16-bit formats too
+    ((12, 12, 12, 24), 33, "full", "f64 f16n"),          # odd above 32: direct in FP64
+    ((16, 16, 16, 32), 3, "full", "f32 f16n"),           # 3 rhs: direct in 16 bits
+    ((16, 16, 16, 32), 11, "even", "f32 f16n"),          # half field, fewer than 12 rhs: direct
+    ((16, 16, 16, 32), 12, "odd", "f64 f32 bf16n"),      # 786,432 points: LDS for FP64 / FP32
+    ((12, 12, 12, 24), 36, "even", "f32 f16n"),          # 746,496: LDS in every format
+])
+def test_pack_routes_agree(dims, nrhs, subset, precs):
+    """wl_pack_spinor through LDS and direct: every right-hand side of a field packed together equals, unpacked, the
+    one packed alone (bit for bit; FP64: the source itself), on both sides of the lines between the routes."""
+    lat = W.Lattice.create(synth.su3_links(dims, 0.3, 741), (1, 1, 1, -1))
+    sub = W.SUBSET[subset]
+    nsite = int(np.prod(dims)) // (1 if subset == "full" else 2)
+    gen = torch.Generator(device="cuda").manual_seed(742)
+    src = torch.view_as_complex(torch.randn((nrhs, nsite, 4, 3, 2), generator=gen, device="cuda", dtype=torch.float64))
+    for name in precs.split():
+        prec = W.PREC[name]
+        out = torch.empty_like(src)
+        W.wl_unpack_spinor(lat.ctx, out, lat.pack(src, sub, prec, nrhs), sub, prec, nrhs)
+        if name == "f64":
+            assert torch.equal(torch.view_as_real(out), torch.view_as_real(src))
+        one = torch.empty_like(src[0])
+        for r in range(0, nrhs, max(1, nrhs // 5)):
+            W.wl_unpack_spinor(lat.ctx, one, lat.pack(src[r], sub, prec), sub, prec, 1)
+            assert torch.equal(torch.view_as_real(out[r]), torch.view_as_real(one)), (name, r)
+    lat.close()
