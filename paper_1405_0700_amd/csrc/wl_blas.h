@@ -120,10 +120,11 @@ struct CGVecSys {
     int *count;                // fold: systems still iterating
     long start;                // first block (set by the launcher)
 };
-struct CGVecArgs {
-    CGVecSys sys[CG_SYS_MAX];
+template <int N> struct CGVecArgsOf {
+    CGVecSys sys[N];
     int nsys;
 };
+using CGVecArgs = CGVecArgsOf<CG_SYS_MAX>;
 hipError_t cg_update_xp(int prec, CGVecArgs &a, bool fold, hipStream_t s);
 // v1 (prec dprec) = v0 (prec sprec), or v1 += v0 if accumulate
 hipError_t blas_convert(int dprec, int sprec, bool accumulate, VecArgs &a, int nhalves, hipStream_t s);

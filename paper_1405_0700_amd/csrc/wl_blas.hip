@@ -164,14 +164,16 @@ __global__ void __launch_bounds__(256) k_cg_p(const VecArgs a) {
 // FP64 and FP32 storage: a thread takes one 16-byte unit of each field (x has the same
 // units), so that a small lattice still fills the chip (8^3x16 FP64: 4.4 us with the
 // beta step against 6.3 us without it and with a thread per point); 16-bit storage: a thread per point.
-__device__ __forceinline__ const CGVecSys &cg_vec_sys(const CGVecArgs &a) {
+// A single solve passes one system's arguments, not eight: 1 KB of kernel arguments costs
+// the host half a microsecond a launch (8^3x16 BF16, launches from the host: 6.5 against 6.8 ms).
+template <int N> __device__ __forceinline__ const CGVecSys &cg_vec_sys(const CGVecArgsOf<N> &a) {
     int k = 0;
-    while (k + 1 < a.nsys && (long)blockIdx.x >= a.sys[k + 1].start) ++k;
+    while (k + 1 < (N == 1 ? 1 : a.nsys) && (long)blockIdx.x >= a.sys[k + 1].start) ++k;
     return a.sys[k];
 }
 
-template <int SP>
-__global__ void __launch_bounds__(256) k_cg_xp(const CGVecArgs A) {
+template <int SP, int N>
+__global__ void __launch_bounds__(256) k_cg_xp(const CGVecArgsOf<N> A) {
     using T = typename SpinorIO<SP>::real;
     const CGVecSys &a = cg_vec_sys(A);
     const long lb = blockIdx.x - a.start, per = (a.n + 255) / 256;
@@ -210,8 +212,8 @@ __device__ __forceinline__ double wave_partials(const double *p, long nblk) {
     return wave_sum(s0 + s1);
 }
 
-template <int SP, bool FOLD>
-__global__ void __launch_bounds__(256) k_cg_xp_unit(const CGVecArgs A) {
+template <int SP, bool FOLD, int N>
+__global__ void __launch_bounds__(256) k_cg_xp_unit(const CGVecArgsOf<N> A) {
     using V = typename std::conditional<SP == WL_F64, double2, float4>::type;
     constexpr int NU = SP == WL_F64 ? 12 : 6;
     __shared__ double s_alpha[FOLD ? 64 : 1], s_beta[FOLD ? 64 : 1];
@@ -641,6 +643,24 @@ hipError_t blas_blockdot(const BlockDotArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_blockdot, dim3((unsigned)blockdot_blocks(a.n)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
+template <int N> static hipError_t launch_xp(int prec, const CGVecArgsOf<N> &a, bool fold, dim3 grid, hipStream_t s) {
+    const dim3 blk(256);
+    switch (prec) {
+    case WL_F64:
+        if (fold) hipLaunchKernelGGL((k_cg_xp_unit<WL_F64, true, N>), grid, blk, 0, s, a);
+        else hipLaunchKernelGGL((k_cg_xp_unit<WL_F64, false, N>), grid, blk, 0, s, a);
+        break;
+    case WL_F32:
+        if (fold) hipLaunchKernelGGL((k_cg_xp_unit<WL_F32, true, N>), grid, blk, 0, s, a);
+        else hipLaunchKernelGGL((k_cg_xp_unit<WL_F32, false, N>), grid, blk, 0, s, a);
+        break;
+    case WL_F16N: hipLaunchKernelGGL((k_cg_xp<WL_F16N, N>), grid, blk, 0, s, a); break;
+    case WL_BF16N: hipLaunchKernelGGL((k_cg_xp<WL_BF16N, N>), grid, blk, 0, s, a); break;
+    case WL_I16N: hipLaunchKernelGGL((k_cg_xp<WL_I16N, N>), grid, blk, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
 hipError_t cg_update_xp(int prec, CGVecArgs &a, bool fold, hipStream_t s) {
     if (a.nsys < 1 || a.nsys > CG_SYS_MAX || (fold && prec != WL_F64 && prec != WL_F32)) return hipErrorInvalidValue;
     const int nu = prec == WL_F64 ? 12 : (prec == WL_F32 ? 6 : 0);
@@ -651,22 +671,9 @@ hipError_t cg_update_xp(int prec, CGVecArgs &a, bool fold, hipStream_t s) {
         y.start = blocks;
         blocks += ((nu ? nu * padded(y.n) : y.n) + 255) / 256 * y.nh;
     }
-    const dim3 grid((unsigned)blocks), blk(256);
-    switch (prec) {
-    case WL_F64:
-        if (fold) hipLaunchKernelGGL((k_cg_xp_unit<WL_F64, true>), grid, blk, 0, s, a);
-        else hipLaunchKernelGGL((k_cg_xp_unit<WL_F64, false>), grid, blk, 0, s, a);
-        break;
-    case WL_F32:
-        if (fold) hipLaunchKernelGGL((k_cg_xp_unit<WL_F32, true>), grid, blk, 0, s, a);
-        else hipLaunchKernelGGL((k_cg_xp_unit<WL_F32, false>), grid, blk, 0, s, a);
-        break;
-    case WL_F16N: hipLaunchKernelGGL(k_cg_xp<WL_F16N>, grid, blk, 0, s, a); break;
-    case WL_BF16N: hipLaunchKernelGGL(k_cg_xp<WL_BF16N>, grid, blk, 0, s, a); break;
-    case WL_I16N: hipLaunchKernelGGL(k_cg_xp<WL_I16N>, grid, blk, 0, s, a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    const dim3 grid((unsigned)blocks);
+    if (a.nsys == 1) return launch_xp(prec, CGVecArgsOf<1>{{a.sys[0]}, 1}, fold, grid, s);
+    return launch_xp(prec, a, fold, grid, s);
 }
 hipError_t blas_scale_by_rho(VecArgs &a, int nh, hipStream_t s) {
     if (!a.sc || a.nrhs != 1) return hipErrorInvalidValue;

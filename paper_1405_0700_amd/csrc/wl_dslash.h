@@ -103,7 +103,8 @@ constexpr double NT_WORKING_SET = 300e6;
 // cached, an FP64 refresh evicts the iterations' fields, which are a quarter of its own; solves
 // with hinted refreshes of 210 to 320 MB are 0.5 to 1.5 % faster (7 lattices from 16x20x24x32
 // to 20x24x24x32 x 3 formats, 21 of 21, medians of 7, runs 0.1 % apart; BF16 at 16x24x28x30,
-// 279 MB, 13.78 against 13.93 ms).  FP32 storage, same lattices: 0.9956 to 1.0035, level.
+// 279 MB, 13.78 against 13.93 ms); with D in place of D_hat, FP16, -0.1 to 1.3 % on six more.
+// FP32 storage, the same lattices: 0.9956 to 1.0035, level.
 constexpr double nt_refresh_limit(int prec) { return prec >= WL_F16N ? 200e6 : NT_WORKING_SET; }
 // whether a launch uses the non-temporal hints
 bool use_nontemporal(int prec, const LaunchCfg &cfg, const HopArgs &a, int nparity, int epi,
