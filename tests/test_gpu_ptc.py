@@ -607,8 +607,8 @@ def test_network_of_tiny_numbers(channels, nrhs, adjoint):
 
 @pytest.mark.parametrize("channels,nrhs,adjoint", [(1, 2, False), (1, 3, True), (9, 2, True), (9, 3, False)])
 def test_networks_on_the_layer_kernels(channels, nrhs, adjoint):
-    """Networks of one or more than eight channels take the layer kernels: M (M^+) of several right-hand sides
-    against the oracle's two layers.  8x6x10x12 x nrhs leaves the gather's last blocks partly empty and their
+    """Networks of one or more than eight channels take the layer kernels (two to eight the matrix cores, padded to
+    four or eight): M (M^+) of several right-hand sides against the oracle's two layers.  8x6x10x12 x nrhs leaves the gather's last blocks partly empty and their
     number no multiple of the eight XCDs."""
     dims = (8, 6, 10, 12)
     ph = random_phases(690 + channels)
@@ -634,7 +634,8 @@ def test_networks_on_the_layer_kernels(channels, nrhs, adjoint):
 
 @pytest.mark.parametrize("channels,dims", [(8, (10, 14, 6, 22)), (3, (10, 14, 6, 22)), (2, (18, 14, 22, 24))])
 def test_gradients_where_blocks_take_several_tiles(channels, dims):
-    """The fused gradient kernel with more than 512 tiles of 16 points, where a block takes several: 10x14x6x22
+    """The fused gradient kernel with more than 512 tiles of 16 points, where a block takes several (the ragged
+    lattices of the test above have at most 72, one a block): 10x14x6x22
     has 1,156 tiles, three a block (the last block one, one block across the parities, a partial tile at the end
     of each parity), 18x14x22x24 has 8,316, sixteen a block (the last block twelve).  A tile left out would be
     1e-4 to 1e-3 of the sum; FP32 arithmetic with the oracle's BF16 weights: TOL32 normwise."""
